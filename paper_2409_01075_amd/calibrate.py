@@ -28,7 +28,12 @@ loads come from HBM.  The launch floor is a K = 0 call of the smallest kernel.
 Writes calib_<arch>.txt next to libvx.so; the library reads it at its first
 plan when it was taken on the same kernel set.
 
-Usage: python -m paper_2409_01075_amd.calibrate [--out PATH] [--dtypes f16,bf16,f32]
+Usage: python -m paper_2409_01075_amd.calibrate [--out PATH] [--dtypes f16,bf16,f32] [--ids 0-5,9]
+
+--ids re-measures only those kernels (the ones whose code a change touched) and
+keeps the rows of all others from the table next to the library, so that
+plans among unchanged kernels do not move with the run-to-run spread of a
+whole new table.
 """
 import argparse
 import ctypes
@@ -71,7 +76,13 @@ def _split_fit(pts):
     return a, b
 
 
-def calibrate(out=None, dtypes=(0, 1, 2), rot_mib=256, verbose=True):
+def _table_rows(path):
+    """{kernel id: its row's values after the id, as text} of a calibration table."""
+    with open(path) as f:
+        return {int(ln.split()[1]): ln.split(None, 2)[2].strip() for ln in f if ln.startswith("kernel ")}
+
+
+def calibrate(out=None, dtypes=(0, 1, 2), rot_mib=256, verbose=True, ids=None):
     import numpy as np
     import torch
     from . import vx
@@ -103,7 +114,7 @@ def calibrate(out=None, dtypes=(0, 1, 2), rot_mib=256, verbose=True):
     t_start = time.time()
     for kid in range(n):
         k = vx.vx_registry_get(kid)
-        if not k.enabled or k.dtype not in dtypes:
+        if not k.enabled or k.dtype not in dtypes or (ids is not None and kid not in ids):
             continue
         occ = vx.vx_kernel_occupancy(kid)
         slots = hw.num_cu * occ
@@ -193,7 +204,13 @@ def calibrate(out=None, dtypes=(0, 1, 2), rot_mib=256, verbose=True):
                                                                      k.family, k.vec), occ, step_full,
                                 step_light, fix_full, fix_light, split_a, split_b, time.time() - t_start),
                   file=sys.stderr, flush=True)
-    out = out or os.path.join(HERE, "calib_%s.txt" % arch)
+    default = os.path.join(HERE, "calib_%s.txt" % arch)
+    lines = {r[0]: "kernel %d %.1f %.1f %.1f %.1f %.5f %.1f %.1f %.1f %.1f\n" % r for r in rows}
+    if ids is not None:
+        for kid, rest in _table_rows(default).items():
+            if kid not in lines and kid < n:
+                lines[kid] = "kernel %d %s\n" % (kid, rest)
+    out = out or default
     with open(out, "w") as f:
         f.write("# vx kernel calibration (offline, per device): written by paper_2409_01075_amd/calibrate.py\n")
         f.write("# kernel <id> <step_full_ns> <fixed_full_ns> <step_light_ns> <fixed_light_ns> <load_light>"
@@ -202,8 +219,8 @@ def calibrate(out=None, dtypes=(0, 1, 2), rot_mib=256, verbose=True):
         f.write("device_cus %d\n" % hw.num_cu)
         f.write("registry_hash %s\n" % vx.vx_registry_hash())
         f.write("launch_ns %.1f\n" % launch)
-        for r in rows:
-            f.write("kernel %d %.1f %.1f %.1f %.1f %.5f %.1f %.1f %.1f %.1f\n" % r)
+        for kid in sorted(lines):
+            f.write(lines[kid])
     if verbose:
         print("wrote %s (%d kernels, launch floor %.0f ns)" % (out, len(rows), launch), file=sys.stderr)
     return out
@@ -213,6 +230,13 @@ if __name__ == "__main__":
     ap = argparse.ArgumentParser()
     ap.add_argument("--out", default=None)
     ap.add_argument("--dtypes", default="f32,f16,bf16")
+    ap.add_argument("--ids", default=None)
     a = ap.parse_args()
+    ids = None
+    if a.ids:
+        ids = set()
+        for part in a.ids.split(","):
+            lo, _, hi = part.partition("-")
+            ids.update(range(int(lo), int(hi or lo) + 1))
     codes = {"f32": 0, "f16": 1, "bf16": 2}
-    calibrate(a.out, tuple(codes[d] for d in a.dtypes.split(",")))
+    calibrate(a.out, tuple(codes[d] for d in a.dtypes.split(",")), ids=ids)

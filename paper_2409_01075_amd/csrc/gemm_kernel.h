@@ -207,6 +207,88 @@ __device__ __forceinline__ void conv_gather(const VxGemmArgs& p, const char* __r
     }
 }
 
+// x shifted down by s bytes (zeros from above), s >= 0.
+__device__ __forceinline__ u32x4 shr_bytes(const u32x4& x, int s)
+{
+    const uint64_t lo = (uint64_t)x[0] | (uint64_t)x[1] << 32, hi = (uint64_t)x[2] | (uint64_t)x[3] << 32;
+    const int t = s * 8;
+    const uint64_t l = t == 0 ? lo : t < 64 ? lo >> t | hi << (64 - t) : t < 128 ? hi >> (t - 64) : 0;
+    const uint64_t h = t < 64 ? hi >> t : 0;
+    return u32x4{(unsigned)l, (unsigned)(l >> 32), (unsigned)h, (unsigned)(h >> 32)};
+}
+// the first `valid` elements of EB bytes of a chunk, zeros after
+template <int EB>
+__device__ __forceinline__ u32x4 keep_elems(const u32x4& x, int valid)
+{
+    u32x4 y;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        if constexpr (EB == 4)
+            y[d] = d < valid ? x[d] : 0u;
+        else
+            y[d] = 2 * d + 1 < valid ? x[d] : 2 * d < valid ? x[d] & 0xffffu : 0u;
+    }
+    return y;
+}
+
+// One K step of one operand for the branch-free loads: the scalar base, and
+// what is added to a thread's chunk offsets and bounds them.  A step wholly
+// inside the slice starts at its own first element; the last step is addressed
+// from the panel's start, with every chunk kept inside the operand: a chunk
+// that would read past its end is read earlier and shifted down afterwards.
+struct StepBase {
+    const char* p;
+    unsigned add, lim;
+};
+// Byte offsets of a thread's chunks within a K step.  Rows past M take the
+// last row and columns past N the row's last column: what they load only
+// reaches outputs that are not stored.  (An element-aligned chunk at the end
+// of a row of A or B reads on into the next row: columns past N, or past
+// the slice, which the store to LDS zeroes.)
+template <class C>
+struct StepOffsets {
+    static constexpr int CPR = C::KB / C::VE;   // A chunks per row
+    static constexpr int NB_ = C::H ? C::BBLK : C::BV;
+    static constexpr int BR = C::H ? C::BK : 1; // rows of B per block
+    static_assert(C::NT % CPR == 0, "a thread's A chunks lie in one chunk column");
+    unsigned a0, a_last, a_step, b[NB_];
+    unsigned a_lim, b_lim;   // last chunk of the panel of A, of the batch's B
+    bool ok;                 // every offset fits 32 bits, and each operand holds a whole chunk
+
+    __device__ __forceinline__ void init(int n0, int Mrel, int N, int K, int t)
+    {
+        const unsigned row = (unsigned)K * C::EB;
+        const int rows = min(Mrel, C::MB);
+        const int64_t a_end = ((int64_t)Mrel * K - C::VE) * C::EB, b_end = ((int64_t)K * N - C::VE) * C::EB;
+        // (offsets of the last step run from the panel's start: up to a K step past the row or matrix)
+        // ... and a row of B holds the elements a chunk at its end reads on past it
+        ok = a_end >= 0 && b_end >= 0 && N >= C::VE && ((int64_t)C::MB * K + C::KB) * C::EB < (1ll << 32) &&
+             ((int64_t)(K + C::KB) * N + C::VE) * C::EB < (1ll << 32);
+        a0 = (unsigned)(t / CPR) * row + (unsigned)(t % CPR) * 16u;
+        a_last = (unsigned)(rows - 1) * row + (unsigned)(t % CPR) * 16u;
+        a_step = (unsigned)(C::NT / CPR) * row;
+        a_lim = (unsigned)(a_end < 0xffffffffll ? a_end : 0xffffffffll);
+        b_lim = (unsigned)b_end;
+#pragma unroll
+        for (int i = 0; i < NB_; ++i) {
+            const int idx = t + i * C::NT;
+            const int k = C::H ? (idx % C::KBB) * C::BK : idx / (C::NB / C::VE);
+            const int c = C::H ? idx / C::KBB : idx % (C::NB / C::VE);
+            b[i] = ((unsigned)k * (unsigned)N + (unsigned)min(n0 + c * C::VE, N - 1)) * C::EB;
+        }
+    }
+    __device__ __forceinline__ unsigned a(int v) const { return min(a0 + (unsigned)v * a_step, a_last); }
+    __device__ __forceinline__ StepBase step_a(const char* Ab, int k0, bool last) const
+    {
+        return last ? StepBase{Ab, (unsigned)k0 * C::EB, a_lim} : StepBase{Ab + (int64_t)k0 * C::EB, 0u, 0xffffffffu};
+    }
+    __device__ __forceinline__ StepBase step_b(const char* Bb, int k0, int N, bool last) const
+    {
+        return last ? StepBase{Bb, (unsigned)k0 * (unsigned)N * C::EB, b_lim}
+                    : StepBase{Bb + (int64_t)k0 * N * C::EB, 0u, 0xffffffffu};
+    }
+};
+
 template <class C>
 struct Tile {
     // ---------------------------------------------------------- Load (level 1)
@@ -291,6 +373,56 @@ struct Tile {
                 }
             }
         }
+    }
+
+    // One K step without a branch: every chunk is one load from an address that
+    // lies inside the operand.  Latency-bound work (small products) waits for
+    // these loads, and a predicated load into zeroed registers (above) makes
+    // the compiler wait for every load in flight before it issues the next one:
+    // the chunks of a step then come one memory round trip after the other.
+    // What the branch-free loads bring from outside the slice is zeroed on the
+    // way into LDS (fix_last).  fp16 777 x 1111 x 533, every row off 16 bytes:
+    // 18.3 -> 9.7 us; fp32 1021 x 3072 x 768, bound by its MFMAs: 51.3 -> 47.8 us.
+    __device__ __forceinline__ void load_a(const StepBase& s, const StepOffsets<C>& so)
+    {
+#pragma unroll
+        for (int v = 0; v < C::AV; ++v)
+            ra[v] = ld_g<u32x4_u>(s.p + min(so.a(v) + s.add, s.lim));
+    }
+    __device__ __forceinline__ void load_b(const StepBase& s, const StepOffsets<C>& so, int N)
+    {
+        constexpr int BR = StepOffsets<C>::BR;
+#pragma unroll
+        for (int i = 0; i < StepOffsets<C>::NB_; ++i)
+#pragma unroll
+            for (int r = 0; r < BR; ++r)
+                rb[i * BR + r] = ld_g<u32x4_u>(s.p + min(so.b[i] + (unsigned)r * (unsigned)N * C::EB + s.add, s.lim));
+    }
+    // The last K step (first column k0) after load_a and load_b: chunks read
+    // ahead of their place shifted down, elements at or past kend zeroed.
+    __device__ __forceinline__ void fix_last(const StepBase& sa, const StepBase& sb, const StepOffsets<C>& so, int k0,
+                                             int kend, int N, int t)
+    {
+        constexpr int BR = StepOffsets<C>::BR;
+#pragma unroll
+        for (int v = 0; v < (C::CONV ? 0 : C::AV); ++v) {
+            const unsigned off = so.a(v) + sa.add;
+            if constexpr (!C::VEC)
+                ra[v] = shr_bytes(ra[v], (int)(off - min(off, sa.lim)));
+            ra[v] = keep_elems<C::EB>(ra[v], kend - k0 - (t % StepOffsets<C>::CPR) * C::VE);
+        }
+#pragma unroll
+        for (int i = 0; i < StepOffsets<C>::NB_; ++i)
+#pragma unroll
+            for (int r = 0; r < BR; ++r) {
+                const int idx = t + i * C::NT;
+                const int k = C::H ? (idx % C::KBB) * C::BK + r : idx / (C::NB / C::VE);
+                const unsigned off = so.b[i] + (unsigned)r * (unsigned)N * C::EB + sb.add;
+                u32x4 x = rb[i * BR + r];
+                if constexpr (!C::VEC)
+                    x = shr_bytes(x, (int)(off - min(off, sb.lim)));
+                rb[i * BR + r] = k0 + k < kend ? x : u32x4{0, 0, 0, 0};
+            }
     }
 
     // A of a convolution: the K step at the chunk column held in `ca`,
@@ -921,43 +1053,83 @@ __device__ __forceinline__ void gemm_body(const VxGemmArgs& args)
     Acc<C> acc;
     acc_zero<C>(acc);
 
-    // PF register sets: set j holds K steps j, j + PF, j + 2 PF, ... on their
-    // way from memory into the LDS stage; the loop is unrolled by PF so that
-    // every set index is a constant
+    // PF register sets (convolutions; a GEMM has one): set j holds K steps j,
+    // j + PF, j + 2 PF, ... on their way from memory into the LDS stage; the
+    // loop is unrolled by PF so that every set index is a constant
+    static_assert(C::CONV || C::PF == 1, "a GEMM has one register set");
     Tile<C> tl[C::PF];
     ConvA<C> ca;
     if constexpr (C::CONV)
         ca.init(p, g.m0, g.kbeg, t);
-    // one K step of A and B into register set s (for a convolution, A through
-    // the im2col map; the steps are loaded in order, so its state just advances)
-    auto load = [&](Tile<C>& s, int k0) {
-        s.load(Ab, Bb, 0, g.n0, k0, g.kend, Mrel, p.N, p.K, t);
-        if constexpr (C::CONV) {
-            s.load_a_conv(p, (const char*)p.A, ca, g.kend);
-            ca.advance(p);
-        }
-    };
-#pragma unroll
-    for (int j = 0; j < C::PF; ++j)
-        if (j < g.nk)
-            load(tl[j], g.kbeg + j * C::KB);
-    if (g.nk > 0)
-        tl[0].store(smem, t);
-    __syncthreads();
-    for (int it0 = 0; it0 < g.nk; it0 += C::PF) {
-#pragma unroll
-        for (int j = 0; j < C::PF; ++j) {
-            const int it = it0 + j;
-            if (it >= g.nk)
-                break;
-            char* cur = smem + (it & 1) * C::STAGE_BYTES;
-            // set j held step it, already in LDS: it takes step it + PF
-            if (it + C::PF < g.nk)
-                load(tl[j], g.kbeg + (it + C::PF) * C::KB);
-            compute_step<C>(cur, acc, wm0, wn0, lane);
-            if (it + 1 < g.nk)
-                tl[(j + 1) % C::PF].store(smem + ((it + 1) & 1) * C::STAGE_BYTES, t);
+    StepOffsets<C> so;
+    so.init(g.n0, Mrel, p.N, p.K, t);
+    if (!C::CONV && so.ok && g.nk > 0) {
+        // A last step is one whose chunks may leave the slice or the operand:
+        // element aligned, also the step that ends exactly at K (its chunks at
+        // the rows' ends read on).
+        const int klast = g.kbeg + (g.nk - 1) * C::KB;
+        const bool fix = klast + C::KB > g.kend || (!C::VEC && g.kend == p.K);
+        Tile<C>& s = tl[0];
+        auto load = [&](int it) {
+            const int k0 = g.kbeg + it * C::KB;
+            const bool last = fix && k0 == klast;
+            s.load_a(so.step_a(Ab, k0, last), so);
+            s.load_b(so.step_b(Bb, k0, p.N, last), so, p.N);
+        };
+        auto to_lds = [&](int it) {
+            if (fix && it == g.nk - 1)
+                s.fix_last(so.step_a(Ab, klast, true), so.step_b(Bb, klast, p.N, true), so, klast, g.kend, p.N, t);
+            s.store(smem + (it & 1) * C::STAGE_BYTES, t);
+        };
+        load(0);
+        to_lds(0);
+        if (g.nk > 1)
+            load(1);
+        __syncthreads();
+        // step it computes from its LDS stage while step it + 1 goes from the
+        // registers into the other stage and step it + 2 is loaded.  (Two or
+        // three register sets, with more steps in flight, measured no faster.)
+        for (int it = 0; it < g.nk - 1; ++it) {
+            to_lds(it + 1);
+            if (it + 2 < g.nk)
+                load(it + 2);
+            compute_step<C>(smem + (it & 1) * C::STAGE_BYTES, acc, wm0, wn0, lane);
             __syncthreads();
+        }
+        compute_step<C>(smem + ((g.nk - 1) & 1) * C::STAGE_BYTES, acc, wm0, wn0, lane);
+        __syncthreads();
+    } else {
+        // one K step into register set s (for a convolution, A through the
+        // im2col map; the steps are loaded in order, so its state just advances)
+        auto load = [&](Tile<C>& s, int k0) {
+            s.load(Ab, Bb, 0, g.n0, k0, g.kend, Mrel, p.N, p.K, t);
+            if constexpr (C::CONV) {
+                s.load_a_conv(p, (const char*)p.A, ca, g.kend);
+                ca.advance(p);
+            }
+        };
+#pragma unroll
+        for (int j = 0; j < C::PF; ++j)
+            if (j < g.nk)
+                load(tl[j], g.kbeg + j * C::KB);
+        if (g.nk > 0)
+            tl[0].store(smem, t);
+        __syncthreads();
+        for (int it0 = 0; it0 < g.nk; it0 += C::PF) {
+#pragma unroll
+            for (int j = 0; j < C::PF; ++j) {
+                const int it = it0 + j;
+                if (it >= g.nk)
+                    break;
+                char* cur = smem + (it & 1) * C::STAGE_BYTES;
+                // set j held step it, already in LDS: it takes step it + PF
+                if (it + C::PF < g.nk)
+                    load(tl[j], g.kbeg + (it + C::PF) * C::KB);
+                compute_step<C>(cur, acc, wm0, wn0, lane);
+                if (it + 1 < g.nk)
+                    tl[(j + 1) % C::PF].store(smem + ((it + 1) & 1) * C::STAGE_BYTES, t);
+                __syncthreads();
+            }
         }
     }
     // the loop ends with a barrier: LDS is idle here

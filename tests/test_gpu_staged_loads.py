@@ -1,0 +1,98 @@
+"""The branch-free loads of the register-staged GEMM kernels at the sizes where
+they can go wrong: K around one and two K steps, rows shorter than a 16-byte
+chunk, a single row or column, the last rows of the operands, batches that end
+exactly at the buffer's end, and values that must not leak from a
+neighbouring row (NaN beside the slice).
+
+Integer-valued operands, so every result is exact and compared bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from oracle import tolerance
+from paper_2409_01075_amd import inputs as I
+from paper_2409_01075_amd import vx
+
+from .gpu_util import from_dev, run_gemm, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _kernels(code):
+    """Element-aligned register-staged GEMM kernels of distinct K steps, and one aligned kernel."""
+    picked = {}
+    for i in range(vx.vx_registry_count()):
+        k = vx.vx_registry_get(i)
+        if k.enabled and k.dtype == code and k.family == 0 and k.op == 0:
+            picked.setdefault((k.kb, k.align), k)
+    return list(picked.values())
+
+
+@pytest.mark.parametrize("code", [I.F32, I.F16, I.BF16])
+def test_edges_of_k_and_n_exact(code):
+    g = I.rng(4100 + code)
+    ve = 4 if code == I.F32 else 8
+    for k in _kernels(code):
+        for K in (1, ve - 1, ve + 1, k.kb - 1, k.kb, k.kb + 1, 2 * k.kb + ve // 2 + 1):
+            for M, N in ((1, 1), (3, ve - 1), (2, ve), (k.mb + 1, ve + 1), (k.mb - 1, k.nb + 1), (1, k.nb + ve)):
+                if k.align == 3:
+                    N, K = -(-N // ve) * ve, -(-K // ve) * ve
+                r = max(1, min(4, I.exact_range(K, code)))
+                A, B = I.small_int(g, (M, K), code, -r, r), I.small_int(g, (K, N), code, -r, r)
+                assert vx.vx_force_plan(k.id, 1) == 0
+                try:
+                    C = run_gemm(A, B, code)
+                finally:
+                    vx.vx_force_plan(-1, 0)
+                tolerance.check_exact(C, oracle.gemm(A, B, code, with_mag=False), code,
+                                      "kernel %d (%d, %d, %d)" % (k.id, M, N, K))
+
+
+@pytest.mark.parametrize("code", [I.F32, I.F16, I.BF16])
+def test_neighbouring_rows_do_not_leak(code):
+    """Row m of A ends beside row m + 1, and a column of B beside the next row:
+    NaN in one row of A or one column of B reaches that row or column of C only."""
+    M, N, K = 5, 11, 37
+    ones = I.to_storage(np.ones((M, K)), code), I.to_storage(np.ones((K, N)), code)
+    nan = np.float32(np.nan) if code == I.F32 else np.uint16(0x7fc0 if code == I.BF16 else 0x7e00)
+    for k in _kernels(code):
+        if k.align:
+            continue
+        A, B = ones[0].copy(), ones[1].copy()
+        A[3, :] = nan
+        B[:, 7] = nan
+        assert vx.vx_force_plan(k.id, 1) == 0
+        try:
+            C = run_gemm(A, B, code)
+        finally:
+            vx.vx_force_plan(-1, 0)
+        v = to_dev(C, code, "cpu").float().numpy()
+        want = np.full((M, N), float(K), dtype=np.float32)
+        want[3, :] = np.nan
+        want[:, 7] = np.nan
+        assert np.array_equal(v, want, equal_nan=True), "kernel %d" % k.id
+
+
+@pytest.mark.parametrize("code", [I.F32, I.F16, I.BF16])
+def test_batch_ending_at_the_buffers_end(code):
+    """Batches back to back and broadcast, the last one ending with its buffer."""
+    g = I.rng(4200 + code)
+    batch, M, N, K = 3, 9, 13, 45
+    A, B = I.small_int(g, (batch, M, K), code, -2, 2), I.small_int(g, (batch, K, N), code, -2, 2)
+    At, Bt = to_dev(A, code), to_dev(B, code)
+    for k in _kernels(code):
+        if k.align:
+            continue
+        for sB in (K * N, 0):
+            Ct = torch.zeros((batch, M, N), dtype=At.dtype, device="cuda")
+            assert vx.vx_force_plan(k.id, 1) == 0
+            st = vx.vx_gemm_batched(batch, M, N, K, code, At.data_ptr(), M * K, Bt.data_ptr(), sB, Ct.data_ptr(), M * N,
+                                    torch.cuda.current_stream().cuda_stream)
+            vx.vx_force_plan(-1, 0)
+            assert st == 0
+            torch.cuda.synchronize()
+            out = from_dev(Ct, code)
+            for b in range(batch):
+                tolerance.check_exact(out[b], oracle.gemm(A[b], B[b if sB else 0], code, with_mag=False), code,
+                                      "kernel %d batch %d" % (k.id, b))
