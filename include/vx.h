@@ -106,7 +106,10 @@ typedef struct vx_kernel_info {
     int schedule;                  /* family 1, level-1 DMA issue: 0 every wave issues its share of
                                       each K step; 1 ping-pong (8 waves, 2 stages): the two halves
                                       of the waves take turns issuing whole K steps while the other
-                                      half starts its MFMAs */
+                                      half starts its MFMAs.  Family 0, fp32: 1 the operands are split
+                                      into three bf16 parts each and multiplied on the bf16 matrix
+                                      cores, accumulated in fp32 (a tile with a value beyond the bf16
+                                      range, or infinite, is computed with the fp32 MFMA) */
 } vx_kernel_info;
 
 /* A concrete execution plan for one call. */

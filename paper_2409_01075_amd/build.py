@@ -54,7 +54,7 @@ def _candidates():
 
 def _kernel_src(part, entries):
     lines = ["// generated by build.py: kernel instantiations, part %d" % part,
-             '#include "gemm_dma.h"', '#include "gemm_valu.h"', "using namespace vxk;", ""]
+             '#include "gemm_dma.h"', '#include "gemm_valu.h"', '#include "gemm_split.h"', "using namespace vxk;", ""]
     for e in entries:
         i = e["id"]
         vec = "true" if e["vec"] else "false"
@@ -67,6 +67,9 @@ def _kernel_src(part, entries):
         elif e["family"] == "valu":
             cfg = "VCfg<%d, %d, %d, %d, %d, %d>" % (e["dt"], e["mb"], e["nb"], e["wn"], e["stages"], e["k_max"])
             body = "gemm_valu_body"
+        elif e.get("schedule", 0) == 1:
+            cfg = "SCfg<%d, %d, %d, %d, %d, %s>" % (e["mb"], e["nb"], e["wm"], e["wn"], e["mi"], vec)
+            body = "gemm_split_body"
         else:
             # stages = K steps in flight in register sets + the LDS stage being computed
             cfg = "Cfg<%d, %d, %d, %d, %d, %d, %d, %s, %s, %d>" % (
@@ -134,7 +137,7 @@ def registry_hash(reg):
     h = hashlib.sha256()
     for e in reg:
         h.update(repr(sorted(e.items())).encode())
-    for f in ("gemm_kernel.h", "gemm_dma.h", "gemm_valu.h", "vx_args.h"):
+    for f in ("gemm_kernel.h", "gemm_dma.h", "gemm_valu.h", "gemm_split.h", "vx_args.h"):
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

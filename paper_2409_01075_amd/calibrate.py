@@ -76,10 +76,12 @@ def _split_fit(pts):
     return a, b
 
 
-def _table_rows(path):
-    """{kernel id: its row's values after the id, as text} of a calibration table."""
+def _table(path):
+    """The launch floor of a calibration table, and {kernel id: its row's values after the id, as text}."""
     with open(path) as f:
-        return {int(ln.split()[1]): ln.split(None, 2)[2].strip() for ln in f if ln.startswith("kernel ")}
+        lines = f.readlines()
+    launch = next(float(ln.split()[1]) for ln in lines if ln.startswith("launch_ns "))
+    return launch, {int(ln.split()[1]): ln.split(None, 2)[2].strip() for ln in lines if ln.startswith("kernel ")}
 
 
 def calibrate(out=None, dtypes=(0, 1, 2), rot_mib=256, verbose=True, ids=None):
@@ -108,6 +110,12 @@ def calibrate(out=None, dtypes=(0, 1, 2), rot_mib=256, verbose=True, ids=None):
     L.vx_gemm(16, 16, 0, 1, None, None, c0.data_ptr(), sp)
     launch = float(np.median([run(lambda i: L.vx_gemm(16, 16, 0, 1, None, None, c0.data_ptr(), sp), 200)
                               for _ in range(3)]))
+
+    default = os.path.join(HERE, "calib_%s.txt" % arch)
+    kept = {}
+    if ids is not None:
+        # the kept rows' fixed times are net of their own table's launch floor
+        launch, kept = _table(default)
 
     rows = []
     n = vx.vx_registry_count()
@@ -204,12 +212,10 @@ def calibrate(out=None, dtypes=(0, 1, 2), rot_mib=256, verbose=True, ids=None):
                                                                      k.family, k.vec), occ, step_full,
                                 step_light, fix_full, fix_light, split_a, split_b, time.time() - t_start),
                   file=sys.stderr, flush=True)
-    default = os.path.join(HERE, "calib_%s.txt" % arch)
     lines = {r[0]: "kernel %d %.1f %.1f %.1f %.1f %.5f %.1f %.1f %.1f %.1f\n" % r for r in rows}
-    if ids is not None:
-        for kid, rest in _table_rows(default).items():
-            if kid not in lines and kid < n:
-                lines[kid] = "kernel %d %s\n" % (kid, rest)
+    for kid, rest in kept.items():
+        if kid not in lines and kid < n and vx.vx_registry_get(kid).enabled:
+            lines[kid] = "kernel %d %s\n" % (kid, rest)
     out = out or default
     with open(out, "w") as f:
         f.write("# vx kernel calibration (offline, per device): written by paper_2409_01075_amd/calibrate.py\n")

@@ -432,6 +432,30 @@ def short_k_candidates(dtype, hw=GFX950):
     return out
 
 
+# fp32 on the bf16 matrix cores (gemm_split.h): every element is split into
+# three bf16 parts on its way into LDS (3 planes of A and B, 2 stages, K step
+# 32), six bf16 MFMAs per product instead of the fp32 MFMA at a sixteenth of
+# their rate.  The splitting and the three planes cost per element moved, so it
+# pays where a tile reuses each element often: 2048^3 runs 98 us on 128 x 128
+# against 144 on the best fp32 tile, 512^3 9.8 us on the smallest of these
+# against 8.2.  Workgroup tiles from 64 x 64; the L0 tile recorded is the fp32
+# one, which the kernels fall back to for values beyond the bf16 range.  Eight
+# or sixteen waves each, so that some split while others multiply (2048^3 on
+# 128 x 128: 108 us with 4 waves, 100 with 8, 98 with 16).
+SPLIT_TILES = ((128, 128, 4, 4, 32), (64, 128, 2, 4, 32), (128, 64, 4, 2, 32), (64, 64, 2, 4, 16))
+
+
+def split_candidates(hw=GFX950):
+    out = []
+    for (mb, nb, wm, wn, mi) in SPLIT_TILES:
+        for vec in (1, 0):
+            e = _entry("f32", "reg", 2, (mb, nb, 32, wm, wn, mi), vec, hw)
+            e["lds"] = max(e["lds"], 2 * 3 * (mb + nb) * 32 * 2)
+            e["schedule"] = 1
+            out.append(e)
+    return out
+
+
 def registry(hw=GFX950):
     """All workgroup-level candidates that are compiled into the library.
 
@@ -442,7 +466,7 @@ def registry(hw=GFX950):
     cannot be DMA'd densely); and a few register-staged 16-byte-aligned tiles
     for very large operands.
     fp32: register-staged tiles, each for 16-byte-aligned and for
-    element-aligned operands."""
+    element-aligned operands, a few of them on the bf16 matrix cores."""
     out = []
     for dtype in ("f16", "bf16"):
         for c in workgroup_tiles(dtype, hw, "dma"):
@@ -471,6 +495,7 @@ def registry(hw=GFX950):
         out += conv_mixed_candidates(dtype, hw)
     for dtype in ("f16", "bf16", "f32"):
         out += conv_candidates(dtype, hw, pf=True)
+    out += split_candidates(hw)
     for i, e in enumerate(out):
         e["id"] = i
     return out

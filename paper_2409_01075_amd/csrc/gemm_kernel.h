@@ -383,20 +383,28 @@ struct Tile {
     // What the branch-free loads bring from outside the slice is zeroed on the
     // way into LDS (fix_last).  fp16 777 x 1111 x 533, every row off 16 bytes:
     // 18.3 -> 9.7 us; fp32 1021 x 3072 x 768, bound by its MFMAs: 51.3 -> 47.8 us.
+    __device__ __forceinline__ void load_a1(const StepBase& s, const StepOffsets<C>& so, int v)
+    {
+        ra[v] = ld_g<u32x4_u>(s.p + min(so.a(v) + s.add, s.lim));
+    }
+    __device__ __forceinline__ void load_b1(const StepBase& s, const StepOffsets<C>& so, int N, int i)
+    {
+        constexpr int BR = StepOffsets<C>::BR;
+#pragma unroll
+        for (int r = 0; r < BR; ++r)
+            rb[i * BR + r] = ld_g<u32x4_u>(s.p + min(so.b[i] + (unsigned)r * (unsigned)N * C::EB + s.add, s.lim));
+    }
     __device__ __forceinline__ void load_a(const StepBase& s, const StepOffsets<C>& so)
     {
 #pragma unroll
         for (int v = 0; v < C::AV; ++v)
-            ra[v] = ld_g<u32x4_u>(s.p + min(so.a(v) + s.add, s.lim));
+            load_a1(s, so, v);
     }
     __device__ __forceinline__ void load_b(const StepBase& s, const StepOffsets<C>& so, int N)
     {
-        constexpr int BR = StepOffsets<C>::BR;
 #pragma unroll
         for (int i = 0; i < StepOffsets<C>::NB_; ++i)
-#pragma unroll
-            for (int r = 0; r < BR; ++r)
-                rb[i * BR + r] = ld_g<u32x4_u>(s.p + min(so.b[i] + (unsigned)r * (unsigned)N * C::EB + s.add, s.lim));
+            load_b1(s, so, N, i);
     }
     // The last K step (first column k0) after load_a and load_b: chunks read
     // ahead of their place shifted down, elements at or past kend zeroed.
@@ -1033,6 +1041,49 @@ struct ConvA {
     }
 };
 
+// The K loop of a register-staged GEMM tile with branch-free loads (so.ok):
+// step it computes from its LDS stage while step it + 1 goes from the
+// registers into the other stage and step it + 2 is loaded.  (Two or three
+// register sets, with more steps in flight, measured no faster.)  Ends with a
+// barrier: LDS is idle.
+template <class C>
+__device__ __forceinline__ void staged_loop(const GridPos& g, const StepOffsets<C>& so, const char* Ab, const char* Bb, int K,
+                                            int N, Tile<C>& s, Acc<C>& acc, char* smem, int t, int lane, int wm0, int wn0)
+{
+    if (g.nk <= 0)
+        return;
+    // A last step is one whose chunks may leave the slice or the operand:
+    // element aligned, also the step that ends exactly at K (its chunks at
+    // the rows' ends read on).
+    const int klast = g.kbeg + (g.nk - 1) * C::KB;
+    const bool fix = klast + C::KB > g.kend || (!C::VEC && g.kend == K);
+    auto load = [&](int it) {
+        const int k0 = g.kbeg + it * C::KB;
+        const bool last = fix && k0 == klast;
+        s.load_a(so.step_a(Ab, k0, last), so);
+        s.load_b(so.step_b(Bb, k0, N, last), so, N);
+    };
+    auto to_lds = [&](int it) {
+        if (fix && it == g.nk - 1)
+            s.fix_last(so.step_a(Ab, klast, true), so.step_b(Bb, klast, N, true), so, klast, g.kend, N, t);
+        s.store(smem + (it & 1) * C::STAGE_BYTES, t);
+    };
+    load(0);
+    to_lds(0);
+    if (g.nk > 1)
+        load(1);
+    __syncthreads();
+    for (int it = 0; it < g.nk - 1; ++it) {
+        to_lds(it + 1);
+        if (it + 2 < g.nk)
+            load(it + 2);
+        compute_step<C>(smem + (it & 1) * C::STAGE_BYTES, acc, wm0, wn0, lane);
+        __syncthreads();
+    }
+    compute_step<C>(smem + ((g.nk - 1) & 1) * C::STAGE_BYTES, acc, wm0, wn0, lane);
+    __syncthreads();
+}
+
 template <class C>
 __device__ __forceinline__ void gemm_body(const VxGemmArgs& args)
 {
@@ -1061,43 +1112,17 @@ __device__ __forceinline__ void gemm_body(const VxGemmArgs& args)
     ConvA<C> ca;
     if constexpr (C::CONV)
         ca.init(p, g.m0, g.kbeg, t);
+    // (one or two steps of aligned operands have nothing to overlap: there the
+    // predicated loads, with less to compute ahead of the first, are up to 5 %
+    // faster on calls of 2-5 us)
     StepOffsets<C> so;
-    so.init(g.n0, Mrel, p.N, p.K, t);
-    if (!C::CONV && so.ok && g.nk > 0) {
-        // A last step is one whose chunks may leave the slice or the operand:
-        // element aligned, also the step that ends exactly at K (its chunks at
-        // the rows' ends read on).
-        const int klast = g.kbeg + (g.nk - 1) * C::KB;
-        const bool fix = klast + C::KB > g.kend || (!C::VEC && g.kend == p.K);
-        Tile<C>& s = tl[0];
-        auto load = [&](int it) {
-            const int k0 = g.kbeg + it * C::KB;
-            const bool last = fix && k0 == klast;
-            s.load_a(so.step_a(Ab, k0, last), so);
-            s.load_b(so.step_b(Bb, k0, p.N, last), so, p.N);
-        };
-        auto to_lds = [&](int it) {
-            if (fix && it == g.nk - 1)
-                s.fix_last(so.step_a(Ab, klast, true), so.step_b(Bb, klast, p.N, true), so, klast, g.kend, p.N, t);
-            s.store(smem + (it & 1) * C::STAGE_BYTES, t);
-        };
-        load(0);
-        to_lds(0);
-        if (g.nk > 1)
-            load(1);
-        __syncthreads();
-        // step it computes from its LDS stage while step it + 1 goes from the
-        // registers into the other stage and step it + 2 is loaded.  (Two or
-        // three register sets, with more steps in flight, measured no faster.)
-        for (int it = 0; it < g.nk - 1; ++it) {
-            to_lds(it + 1);
-            if (it + 2 < g.nk)
-                load(it + 2);
-            compute_step<C>(smem + (it & 1) * C::STAGE_BYTES, acc, wm0, wn0, lane);
-            __syncthreads();
-        }
-        compute_step<C>(smem + ((g.nk - 1) & 1) * C::STAGE_BYTES, acc, wm0, wn0, lane);
-        __syncthreads();
+    bool whole = false;
+    if (!C::CONV && (!C::VEC || g.nk > 2)) {
+        so.init(g.n0, Mrel, p.N, p.K, t);
+        whole = so.ok;
+    }
+    if (whole) {
+        staged_loop<C>(g, so, Ab, Bb, p.K, p.N, tl[0], acc, smem, t, lane, wm0, wn0);
     } else {
         // one K step into register set s (for a convolution, A through the
         // im2col map; the steps are loaded in order, so its state just advances)

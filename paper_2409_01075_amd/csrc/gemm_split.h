@@ -1,0 +1,264 @@
+// fp32 GEMM on the bf16 matrix cores (gfx950): every operand element is split
+// into three bf16 parts as it goes into LDS, and the products of the parts are
+// accumulated in fp32.
+//
+// a = a0 + a1 + a2 with a0 = bf16(a), a1 = bf16(a - a0), a2 = bf16(a - a0 - a1),
+// each rounded to nearest even, so |a1| <= 2^-9 |a|, |a2| <= 2^-18 |a| and the
+// rest is at most 2^-27 |a| (both differences are exact).  Of the nine products
+// the six of weight down to 2^-18 are taken; the three left out and the rests
+// are at most 2^-25 |a b| together, below the half unit 2^-24 that the fp32
+// product itself may be rounded by.  (The scheme of Henry, Tang and Heinecke,
+// "Leveraging the bfloat16 artificial intelligence datatype for higher-precision
+// computations", ARITH 2019, with its six-product sum.)  A sum of 32 products
+// is rounded into the accumulator once per MFMA, six times per 32 k, where
+// the fp32 MFMA rounds it every 4 k.
+//
+// What bounds it: the fp32 MFMA does 256 FLOP per clock and CU, the bf16 one
+// 4096, so six of them per product do 683.  The splitting costs 5.5 vector
+// instructions per element and step, and the three planes 1.5 times the LDS
+// traffic of fp32; both run beside other waves' MFMAs, so sixteen waves share
+// the largest tile.  2048^3: 144 us on the best fp32 tile, 98 us on 128 x 128
+// (MFMAs and fragment reads alone 60, everything but the MFMAs 64);
+// 1021 x 3072 x 768: 51.3 -> 34.1 us.  Splitting a chunk between groups of
+// MFMAs, or a second register set of loads, measured no faster.
+//
+// Elements the split cannot represent: above the largest bf16 (infinities
+// among them) a0 is infinite and a1 not a number, which every sum they enter
+// shows; below 2^-100 the third part would be subnormal, which the bf16 MFMA
+// takes as zero, so the smallest magnitude is tracked.  A workgroup that met
+// either computes its tile again with the fp32 MFMA, which the kernel keeps.
+// (A test inside the K loop, to turn back early, cost every tile 12 %.)
+#pragma once
+#include "gemm_dma.h"
+
+namespace vxk {
+
+template <int MB_, int NB_, int WM_, int WN_, int MI_, bool VEC_>
+struct SCfg {
+    typedef Cfg<DT_F32, MB_, NB_, 32, WM_, WN_, MI_, VEC_> N;   // the fp32 tile: loads, epilogue, fallback
+    static constexpr int MB = MB_, NB = NB_, KB = 32, MI = MI_, NT = N::NT, DT = DT_F32, EB = 4;
+    static constexpr int KI = MI == 16 ? 32 : 16;
+    static constexpr int CPB = NB / 8;                           // 16-byte bf16 chunks per row of B
+    static constexpr int A_PLANE = MB * KB * 2, B_PLANE = KB * NB * 2;
+    static constexpr int STAGE_BYTES = 3 * (A_PLANE + B_PLANE);
+    static constexpr int LDS_BYTES = 2 * STAGE_BYTES > N::LDS_BYTES ? 2 * STAGE_BYTES : N::LDS_BYTES;
+    static_assert(LDS_BYTES <= 159 * 1024, "LDS budget of one CU, less 1 KiB for the split-K flag");
+};
+
+// Four fp32 values -> their three bf16 parts, packed.
+__device__ __forceinline__ void split3(const u32x4& x, u32x2& p0, u32x2& p1, u32x2& p2)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        f32x2 a = {__uint_as_float(x[2 * h]), __uint_as_float(x[2 * h + 1])};
+        unsigned w[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            w[i] = __builtin_bit_cast(unsigned, __builtin_convertvector(a, bf16x2));
+            a[0] -= __uint_as_float(w[i] << 16);
+            a[1] -= __uint_as_float(w[i] & 0xffff0000u);
+        }
+        p0[h] = w[0];
+        p1[h] = w[1];
+        p2[h] = w[2];
+    }
+}
+
+// A rows are 64 bytes (4 chunks): four rows share the 256-byte bank window and
+// the XOR runs over groups of four rows, so 16 rows of one chunk fill it.
+__device__ __forceinline__ int swz_a4(int m) { return (m >> 2) & 3; }
+
+// The smallest non-zero magnitude a thread has met, as 2 |bits| - 1 (zero wraps
+// to the top).
+struct SplitRange {
+    unsigned mn = ~0u;
+
+    __device__ __forceinline__ void add(const u32x4& x)
+    {
+        mn = min(min(mn, (x[0] << 1) - 1u), (x[1] << 1) - 1u);
+        mn = min(min(mn, (x[2] << 1) - 1u), (x[3] << 1) - 1u);
+    }
+    __device__ __forceinline__ bool tiny() const { return mn < ((127u - 100u) << 24) - 1u; }   // below 2^-100
+};
+
+// Chunk u of a thread's K step (A's AV chunks, then B's BV) from its registers
+// into an LDS stage, split.
+template <class S>
+__device__ __forceinline__ void split_put(const Tile<typename S::N>& tl, lds_char* stage, int u, int t, SplitRange& range)
+{
+    typedef typename S::N N;
+    u32x4 x;
+    lds_char* dst;
+    int plane;
+    if (u < N::AV) {
+        const int idx = t + u * N::NT, r = idx / 8, c = idx % 8;
+        x = tl.ra[u];
+        dst = stage + r * 64 + (((c >> 1) ^ swz_a4(r)) << 4) + (c & 1) * 8;
+        plane = S::A_PLANE;
+    } else {
+        const int idx = t + (u - N::AV) * N::NT, c = idx % (N::NB / 4), k = idx / (N::NB / 4);
+        x = tl.rb[u - N::AV];
+        dst = stage + 3 * S::A_PLANE + k * (N::NB * 2) + (b_pos<S::CPB, S::MI>(c >> 1, k) << 4) + (c & 1) * 8;
+        plane = S::B_PLANE;
+    }
+    u32x2 p0, p1, p2;
+    split3(x, p0, p1, p2);
+    range.add(x);
+    *(lds_u32x2*)dst = p0;
+    *(lds_u32x2*)(dst + plane) = p1;
+    *(lds_u32x2*)(dst + 2 * plane) = p2;
+}
+
+// Part p of the fragments of MFMA step kk of an LDS stage.
+template <class S>
+__device__ __forceinline__ void split_frags(lds_char* stage, u32x4 (&fa)[S::N::FM], u32x4 (&fb)[S::N::FN], int kk, int p, int wm0,
+                                            int wn0, int lane)
+{
+    typedef typename S::N N;
+    constexpr int MI = S::MI, KI = S::KI;
+    const int li = lane % MI, lg = lane / MI;
+    const int s = lane & 15, grp = lane >> 4;
+    const int tr_n = (MI == 16 ? 0 : 16 * (grp & 1)) + 4 * (s & 3);
+    const int tr_k = (MI == 16 ? 8 * grp : 8 * (grp >> 1)) + (s >> 2);
+#pragma unroll
+    for (int fm = 0; fm < N::FM; ++fm) {
+        const int m = wm0 + fm * MI + li;
+        fa[fm] = *(lds_u32x4*)(stage + p * S::A_PLANE + m * 64 + (((kk * (KI / 8) + lg) ^ swz_a4(m)) << 4));
+    }
+#pragma unroll
+    for (int fn = 0; fn < N::FN; ++fn) {
+        const int n = wn0 + fn * MI + tr_n;
+        const int k1 = kk * KI + tr_k, k2 = k1 + 4;
+        lds_char* b = stage + 3 * S::A_PLANE + p * S::B_PLANE + (n & 7) * 2;
+        const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_v4i16*)(b + k1 * (S::NB * 2) + (b_pos<S::CPB, MI>(n >> 3, k1) << 4)));
+        const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_v4i16*)(b + k2 * (S::NB * 2) + (b_pos<S::CPB, MI>(n >> 3, k2) << 4)));
+        const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+        fb[fn] = u32x4{l2[0], l2[1], h2[0], h2[1]};
+    }
+}
+
+// The MFMAs of one LDS stage.  The six products run smallest first, each over
+// all of the wavefront's tiles, so consecutive MFMAs do not depend on each other.
+template <class S>
+__device__ __forceinline__ void split_compute(lds_char* stage, Acc<typename S::N>& acc, int wm0, int wn0, int lane)
+{
+    typedef typename S::N N;
+    constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+    for (int kk = 0; kk < S::KB / S::KI; ++kk) {
+        u32x4 fa[3][N::FM], fb[3][N::FN];
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            split_frags<S>(stage, fa[p], fb[p], kk, p, wm0, wn0, lane);
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+#pragma unroll
+            for (int fn = 0; fn < N::FN; ++fn)
+#pragma unroll
+                for (int fm = 0; fm < N::FM; ++fm) {
+                    if constexpr (S::MI == 16)
+                        mfma16<DT_BF16, 16>(fb[PB[q]][fn], fa[PA[q]][fm], acc.v[fn][fm]);
+                    else
+                        mfma32<DT_BF16>(fb[PB[q]][fn], fa[PA[q]][fm], acc.v[fn][fm]);
+                }
+    }
+}
+
+template <class S>
+__device__ __forceinline__ void gemm_split_body(const VxGemmArgs& args)
+{
+    typedef typename S::N N;
+    VxGemmArgs p = pin_args(args);
+    __shared__ __attribute__((aligned(1024))) char smem[S::LDS_BYTES];
+    const int t = threadIdx.x;
+    const int lane = t & 63, wave = t >> 6;
+    const GridPos g = grid_pos<N::MB, N::NB, N::KB>(p);
+    const char* Ab = (const char*)p.A + ((int64_t)g.b * p.sA + (int64_t)g.m0 * p.K) * 4;
+    const char* Bb = (const char*)p.B + (int64_t)g.b * p.sB * 4;
+    const int Mrel = p.M - g.m0;
+    const int wm0 = (wave % (N::MB / N::MW)) * N::MW, wn0 = (wave / (N::MB / N::MW)) * N::NW;
+
+    Acc<N> acc;
+    acc_zero<N>(acc);
+    Tile<N> s;
+    StepOffsets<N> so;
+    so.init(g.n0, Mrel, p.N, p.K, t);
+    if (so.ok && g.nk > 0) {
+        const int klast = g.kbeg + (g.nk - 1) * N::KB;
+        const bool fix = klast + N::KB > g.kend || (!N::VEC && g.kend == p.K);
+        SplitRange range;
+        auto load = [&](int it) {
+            const int k0 = g.kbeg + it * N::KB;
+            const bool last = fix && k0 == klast;
+            s.load_a(so.step_a(Ab, k0, last), so);
+            s.load_b(so.step_b(Bb, k0, p.N, last), so, p.N);
+        };
+        auto stage = [&](int it) { return (lds_char*)smem + (it & 1) * S::STAGE_BYTES; };
+        auto to_lds = [&](int it) {
+#pragma unroll
+            for (int u = 0; u < N::AV + N::BV; ++u)
+                split_put<S>(s, stage(it), u, t, range);
+        };
+        auto fix_last = [&]() {
+            if (fix)
+                s.fix_last(so.step_a(Ab, klast, true), so.step_b(Bb, klast, p.N, true), so, klast, g.kend, p.N, t);
+        };
+        load(0);
+        if (g.nk == 1)
+            fix_last();
+        to_lds(0);
+        if (g.nk > 1)
+            load(1);
+        __syncthreads();
+        // step it computes while step it + 1 is split into the other stage and
+        // step it + 2 is loaded; the last but one iteration stands apart for its
+        // fix_last
+        for (int it = 0; it + 2 < g.nk; ++it) {
+            to_lds(it + 1);
+            load(it + 2);
+            split_compute<S>(stage(it), acc, wm0, wn0, lane);
+            __syncthreads();
+        }
+        if (g.nk > 1) {
+            fix_last();
+            to_lds(g.nk - 1);
+            split_compute<S>(stage(g.nk - 2), acc, wm0, wn0, lane);
+            __syncthreads();
+        }
+        split_compute<S>(stage(g.nk - 1), acc, wm0, wn0, lane);
+        bool finite = true;
+#pragma unroll
+        for (int fn = 0; fn < N::FN; ++fn)
+#pragma unroll
+            for (int fm = 0; fm < N::FM; ++fm)
+#pragma unroll
+                for (int e = 0; e < N::ACC; ++e)
+                    finite = finite && __builtin_isfinite(acc.v[fn][fm][e]);
+        // (also ends the reads of the LDS stages)
+        if (__syncthreads_or(range.tiny() || !finite)) {
+            acc_zero<N>(acc);
+            staged_loop<N>(g, so, Ab, Bb, p.K, p.N, s, acc, smem, t, lane, wm0, wn0);
+        }
+    }
+    if (!so.ok) {
+        for (int it = 0; it < g.nk; ++it) {
+            s.load(Ab, Bb, 0, g.n0, g.kbeg + it * N::KB, g.kend, Mrel, p.N, p.K, t);
+            s.store(smem, t);
+            __syncthreads();
+            compute_step<N>(smem, acc, wm0, wn0, lane);
+            __syncthreads();
+        }
+    }
+    if (g.split > 1 && !reduce_split<N>(p, acc, g, t))
+        return;
+    if constexpr (N::MB * N::LDC * 4 <= S::LDS_BYTES)
+        store_lds<N>(p, acc, g, t, lane, wm0, wn0, (lds_char*)smem);
+    else
+        store_direct<N>(p, acc, g, lane, wm0, wn0);
+}
+
+}  // namespace vxk

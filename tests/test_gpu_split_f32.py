@@ -1,0 +1,106 @@
+"""fp32 GEMM on the bf16 matrix cores (operands in three bf16 parts): against
+binary64 with the error of the fp32 MFMA as the measure, over magnitudes, at
+the edges of its tiles, and with the values the parts cannot hold."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from oracle import tolerance
+from paper_2409_01075_amd import inputs as I
+from paper_2409_01075_amd import vx
+
+from .gpu_util import run_gemm
+
+pytestmark = pytest.mark.gpu
+
+
+def _split_kernels():
+    ks = [vx.vx_registry_get(i) for i in range(vx.vx_registry_count())]
+    return [k for k in ks if k.enabled and k.dtype == I.F32 and k.family == 0 and k.op == 0 and k.schedule == 1]
+
+
+def _native_like(k):
+    """An fp32-MFMA kernel of the same alignment class."""
+    ks = [vx.vx_registry_get(i) for i in range(vx.vx_registry_count())]
+    return next(n for n in ks if n.enabled and n.dtype == I.F32 and n.family == 0 and n.op == 0 and n.schedule == 0 and
+                n.align == k.align and n.mb == 64 and n.nb == 64)
+
+
+def _forced(k, A, B, split=1):
+    assert vx.vx_force_plan(k.id, split) == 0
+    try:
+        return run_gemm(A, B, I.F32)
+    finally:
+        vx.vx_force_plan(-1, 0)
+
+
+def test_there_are_split_kernels_of_both_alignments():
+    assert {k.align for k in _split_kernels()} == {0, 3}
+
+
+@pytest.mark.parametrize("K", [1, 31, 32, 33, 64, 65, 97, 800])
+def test_no_less_precise_than_the_fp32_mfma(K):
+    """2-norm error against binary64, tile edges in M and N; at most the fp32
+    kernel's (with a floor of one part in 2^24 for results that both round to
+    almost every bit), and every element within the fp32 bound."""
+    g = I.rng(5200 + K)
+    for k in _split_kernels():
+        Kk = -(-K // 4) * 4 if k.align == 3 else K
+        M, N = k.mb + 5, k.nb + 12
+        A, B = I.normal(g, (M, Kk), I.F32), I.normal(g, (Kk, N), I.F32, 0.02)
+        ref, mag = oracle.gemm(A, B, I.F32)
+        for split in (1, 2):
+            if split * 32 >= Kk + 32:
+                continue
+            C = _forced(k, A, B, split)
+            tolerance.check(C, ref, mag, I.F32, "kernel %d K %d split %d" % (k.id, Kk, split))
+            err = np.linalg.norm(C - ref) / np.linalg.norm(ref)
+            nat = np.linalg.norm(_forced(_native_like(k), A, B, split) - ref) / np.linalg.norm(ref)
+            assert err <= max(1.05 * nat, 2.0 ** -24), (k.id, Kk, split, err, nat)
+
+
+@pytest.mark.parametrize("sa,sb", [(1e-29, 1.0), (1e-30, 1e10), (1e-18, 1e-18), (1e18, 1e18), (1e-37, 1e30), (1e-40, 1e30),
+                                   (3e37, 1e-5)])
+def test_magnitudes(sa, sb):
+    """Scaled operands: parts that would be subnormal, subnormal inputs, values near the largest fp32."""
+    g = I.rng(5300)
+    M, N, K = 70, 68, 100
+    A = (I.normal(g, (M, K), I.F32).astype(np.float64) * sa).astype(np.float32)
+    B = (I.normal(g, (K, N), I.F32).astype(np.float64) * sb).astype(np.float32)
+    ref, mag = oracle.gemm(A, B, I.F32)
+    for k in _split_kernels():
+        tolerance.check(_forced(k, A, B), ref, mag, I.F32, "kernel %d scales %g %g" % (k.id, sa, sb))
+
+
+def test_one_tiny_value_late_in_k():
+    """A single subnormal in a late K step still counts: its row's only product."""
+    M, N, K = 64, 64, 32 * 11 + 4
+    A, B = np.zeros((M, K), np.float32), np.full((K, N), 2.0 ** 20, np.float32)
+    A[7, K - 2] = np.float32(2.0 ** -140 + 2.0 ** -149)
+    want = (A.astype(np.float64) @ B.astype(np.float64)).astype(np.float32)
+    assert want[7, 0] != 0
+    for k in _split_kernels():
+        assert np.array_equal(_forced(k, A, B), want), "kernel %d" % k.id
+
+
+def test_infinities_nan_and_the_largest_values():
+    """An infinity, NaN or a value above the largest bf16 gives what the fp32
+    MFMA gives: no NaN that the sum does not hold, and exact where it is exact."""
+    M, N, K = 66, 68, 40
+    big = np.float32(3.402e38)
+    A, B = np.ones((M, K), np.float32), np.ones((K, N), np.float32)
+    A[1, 3] = np.inf
+    A[2, 5] = -np.inf
+    A[3, 7] = np.nan
+    A[4, :] = 0.0
+    A[4, 9] = big          # above the largest bf16; the row's only product
+    A[5, 0], A[5, 1] = np.inf, -np.inf
+    B[11, 10] = np.inf
+    B[12, 11] = 0.0
+    want = A.astype(np.float64) @ B.astype(np.float64)
+    with np.errstate(over="ignore"):
+        want = want.astype(np.float32)
+    for k in _split_kernels():
+        C = _forced(k, A, B)
+        assert np.array_equal(C, want, equal_nan=True), "kernel %d" % k.id
