@@ -241,10 +241,13 @@ struct StepBase {
     unsigned add, lim;
 };
 // Byte offsets of a thread's chunks within a K step.  Rows past M take the
-// last row and columns past N the row's last column: what they load only
-// reaches outputs that are not stored.  (An element-aligned chunk at the end
-// of a row of A or B reads on into the next row: columns past N, or past
-// the slice, which the store to LDS zeroes.)
+// last row and columns past N the row's last chunk (element aligned: its last
+// column): what they load only reaches outputs that are not stored.  (An
+// element-aligned chunk at the end of a row of A or B reads on into the next
+// row: columns past N, or past the slice, which the store to LDS zeroes.  In
+// the last row of B it would read on past the operand, so the step that ends
+// at K is always a last step there, with every chunk kept inside.  An aligned
+// chunk never reads past its row, and needs no such step.)
 template <class C>
 struct StepOffsets {
     static constexpr int CPR = C::KB / C::VE;   // A chunks per row
@@ -274,7 +277,7 @@ struct StepOffsets {
             const int idx = t + i * C::NT;
             const int k = C::H ? (idx % C::KBB) * C::BK : idx / (C::NB / C::VE);
             const int c = C::H ? idx / C::KBB : idx % (C::NB / C::VE);
-            b[i] = ((unsigned)k * (unsigned)N + (unsigned)min(n0 + c * C::VE, N - 1)) * C::EB;
+            b[i] = ((unsigned)k * (unsigned)N + (unsigned)min(n0 + c * C::VE, C::VEC ? N - C::VE : N - 1)) * C::EB;
         }
     }
     __device__ __forceinline__ unsigned a(int v) const { return min(a0 + (unsigned)v * a_step, a_last); }

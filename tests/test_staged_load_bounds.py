@@ -1,0 +1,102 @@
+"""Every chunk address of the register-staged kernels' branch-free loads lies
+inside its operand: the address code of gemm_kernel.h (Cfg, StepBase,
+StepOffsets) compiled for the CPU and run for every thread, chunk and K step
+over K, N and split edges of aligned and element-aligned tiles."""
+import os
+import subprocess
+
+from paper_2409_01075_amd import build as vx_build
+
+_MAIN = r"""
+#include <algorithm>
+#include <cstdint>
+#include <cstdio>
+using std::min;
+enum { DT_F32 = 0, DT_F16 = 1, DT_BF16 = 2 };
+%s
+template <class C>
+static int check(int M, int N, int K, int kbeg, int kend)
+{
+    const int64_t a_bytes = (int64_t)M * K * C::EB, b_bytes = (int64_t)K * N * C::EB;
+    const int nk = (kend - kbeg + C::KB - 1) / C::KB, klast = kbeg + (nk - 1) * C::KB;
+    const bool fix = klast + C::KB > kend || (!C::VEC && kend == K);
+    int bad = 0;
+    for (int m0 = 0; m0 < M; m0 += C::MB)
+        for (int n0 = 0; n0 < N; n0 += C::NB)
+            for (int t = 0; t < C::NT; ++t) {
+                StepOffsets<C> so;
+                so.init(n0, M - m0, N, K, t);
+                if (!so.ok)
+                    continue;
+                const char* Ab = (const char*)((uintptr_t)1 << 40);
+                const char* Bb = (const char*)((uintptr_t)1 << 44);
+                for (int it = 0; it < nk; ++it) {
+                    const int k0 = kbeg + it * C::KB;
+                    const bool last = fix && k0 == klast;
+                    const StepBase sa = so.step_a(Ab, k0, last), sb = so.step_b(Bb, k0, N, last);
+                    for (int v = 0; v < C::AV; ++v) {
+                        const int64_t off = (sa.p - Ab) + min(so.a(v) + sa.add, sa.lim);
+                        bad += off < 0 || (int64_t)m0 * K * C::EB + off + 16 > a_bytes || (C::VEC && off %% 16);
+                    }
+                    for (int i = 0; i < StepOffsets<C>::NB_; ++i)
+                        for (int r = 0; r < StepOffsets<C>::BR; ++r) {
+                            const int64_t off = (sb.p - Bb) + min(so.b[i] + (unsigned)r * (unsigned)N * C::EB + sb.add, sb.lim);
+                            bad += off < 0 || off + 16 > b_bytes || (C::VEC && off %% 16);
+                        }
+                }
+            }
+    if (bad)
+        printf("dt %%d vec %%d tile %%dx%%dx%%d: M %%d N %%d K %%d slice %%d..%%d: %%d chunks outside or misaligned\n", C::DT,
+               (int)C::VEC, C::MB, C::NB, C::KB, M, N, K, kbeg, kend, bad);
+    return bad;
+}
+template <class C>
+static int edges()
+{
+    const int q = C::VEC ? C::VE : 1;
+    auto up = [&](int x) { return (x + q - 1) / q * q; };
+    const int Ks[] = {1, C::VE + 1, C::KB - 1, C::KB, C::KB + 1, 2 * C::KB, 3 * C::KB, 3 * C::KB + 5, 4 * C::KB};
+    const int Ns[] = {1, C::VE, C::VE + 1, C::NB - 1, C::NB, C::NB + 1, C::NB + C::VE};
+    int bad = 0;
+    for (int K : Ks)
+        for (int N : Ns)
+            for (int M : {1, C::MB - 1, C::MB + 1}) {
+                const int k = up(K), n = up(N);
+                bad += check<C>(M, n, k, 0, k);
+                for (int cut = C::KB; cut < k; cut += C::KB) {
+                    bad += check<C>(M, n, k, 0, cut);
+                    bad += check<C>(M, n, k, cut, k);
+                }
+            }
+    return bad;
+}
+int main()
+{
+    int bad = 0;
+    bad += edges<Cfg<DT_F16, 64, 64, 64, 2, 2, 16, false>>() + edges<Cfg<DT_F16, 64, 64, 64, 2, 2, 16, true>>();
+    bad += edges<Cfg<DT_BF16, 128, 64, 64, 2, 2, 32, false>>() + edges<Cfg<DT_BF16, 128, 64, 64, 2, 2, 32, true>>();
+    bad += edges<Cfg<DT_F32, 32, 32, 32, 2, 2, 16, false>>() + edges<Cfg<DT_F32, 32, 32, 32, 2, 2, 16, true>>();
+    bad += edges<Cfg<DT_F32, 64, 128, 32, 2, 4, 32, false>>() + edges<Cfg<DT_F32, 64, 128, 32, 2, 4, 32, true>>();
+    return bad != 0;
+}
+"""
+
+
+def _struct(src, name, template):
+    """The definition of a struct, with its template line."""
+    at = src.index("struct %s {" % name)
+    if template:
+        at = src.rindex("template", 0, at)
+    return src[at:src.index("\n};\n", at) + 4]
+
+
+def test_every_chunk_lies_inside_its_operand(tmp_path):
+    with open(os.path.join(vx_build.CSRC, "gemm_kernel.h")) as f:
+        src = f.read()
+    parts = _struct(src, "Cfg", True) + _struct(src, "StepBase", False) + _struct(src, "StepOffsets", True)
+    parts = parts.replace("__device__", "").replace("__forceinline__", "inline")
+    cpp, exe = tmp_path / "bounds.cpp", tmp_path / "bounds"
+    cpp.write_text(_MAIN % parts)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-o", str(exe), str(cpp)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stdout[:2000]
