@@ -622,8 +622,9 @@ vx_status conv_shape(const vx_conv2d_desc* d, VxShape* sh, VxGemmArgs* a, bool* 
     // the kernels that gather the image through VGPRs load a 16-byte chunk
     // (ve consecutive k) as one vector when the channels come in whole chunks,
     // or when, with unit width dilation, the chunk stays inside the kw * c_in
-    // contiguous elements of one filter row; otherwise element by element.
-    // Chunk starts fall evenly over a filter row, so (ve - 1) of every kw * c_in
+    // contiguous elements of one filter row, and as two vectors when it crosses
+    // into the next; with the width dilated, or filter rows below a chunk,
+    // element by element.  A crossing chunk is priced as the latter.  Chunk starts fall evenly over a filter row, so (ve - 1) of every kw * c_in
     // positions cross its end (taps in the padding aside)
     {
         const int ve = 16 / elem_bytes(d->dtype);

@@ -373,6 +373,7 @@ struct DmaTile {
 template <class C>
 struct VgOperand {
     u32x4 r[C::VGC > 0 ? C::VGC : 1];
+    ConvRegs<(C::CONV && C::VGC > 0 ? C::VGC : 1)> rc;   // a convolution's image
 
     __device__ __forceinline__ static u32x4 gather(const char* p, int valid)
     {
@@ -418,11 +419,13 @@ struct VgOperand {
     __device__ __forceinline__ void load_conv(const VxGemmArgs& p, const char* X, const CA& ca, int kend)
     {
         static_assert(C::VG == 1 && C::CONV, "the image through VGPRs");
-        conv_gather<CA, C::VGC, 8, true, 2>(p, X, ca, kend, r);
+        conv_gather<CA, C::VGC, 8, true, 2>(p, X, ca, kend, rc);
     }
 
-    __device__ __forceinline__ void store(lds_char* stage, int t) const
+    __device__ __forceinline__ void store(lds_char* stage, int t)
     {
+        if constexpr (C::CONV)
+            conv_finish<C::VGC, 8, 2>(rc);
 #pragma unroll
         for (int v = 0; v < C::VGC; ++v) {
             const int idx = t + v * C::NT;
@@ -434,7 +437,12 @@ struct VgOperand {
                 const int kk = idx / C::CPB, c = idx % C::CPB;
                 dst = stage + C::A_BYTES + kk * (C::NB * 2) + (b_pos<C::CPB, C::MI>(c, kk) << 4);
             }
-            *(lds_u32x4*)dst = r[v];
+            u32x4 x;
+            if constexpr (C::CONV)
+                x = rc.x[v];
+            else
+                x = r[v];
+            *(lds_u32x4*)dst = x;
         }
     }
 };

@@ -123,90 +123,6 @@ __device__ __forceinline__ unsigned elem16(const u32x4& v, int j)
     return (j & 1) ? hi16(w) : lo16(w);
 }
 
-// A of a convolution for one K step: the chunk column held in `ca` (see
-// ConvA) of AV rows, gathered from the image X through the im2col map.  Row gm
-// of the implicit A is output pixel (n, oh, ow); column gk is filter tap
-// (kh, kw) and input channel ci, with gk = (kh * KW + kw) * Cin + ci.  When
-// Cin is a multiple of the chunk, a chunk never straddles two taps and is one
-// 16-byte load (or zeros in the padding); otherwise it is gathered element by
-// element, except where it stays inside one filter row (see below).  Taps in
-// the padding and k at or past kend read as zeros.
-template <class CA, int AV, int VE, bool H, int EB>
-__device__ __forceinline__ void conv_gather(const VxGemmArgs& p, const char* __restrict__ X, const CA& ca, int kend,
-                                            u32x4 (&ra)[AV])
-{
-    if (p.cC % VE == 0) {   // wave-uniform: a chunk is VE channels of one tap
-        const int dh = ca.kh * p.cdh, dw = ca.kw * p.cdw;
-        const int64_t koff = ((int64_t)dh * p.cW + dw) * p.cC + ca.ci;
-        const bool kin = ca.gk < kend;
-#pragma unroll
-        for (int v = 0; v < AV; ++v) {
-            u32x4 x = {0, 0, 0, 0};
-            if (kin && (unsigned)(ca.ih0[v] + dh) < (unsigned)p.cH && (unsigned)(ca.iw0[v] + dw) < (unsigned)p.cW)
-                x = ld_g<u32x4_u>(X + (ca.pix[v] + koff) * EB);
-            ra[v] = x;
-        }
-        return;
-    }
-    // channels not a multiple of the chunk: the VE elements of a chunk walk
-    // over channels, then filter columns, then filter rows
-    int ci = ca.ci, kw = ca.kw, kh = ca.kh;
-    int dhe[VE], dwe[VE];
-    int64_t koff[VE];
-#pragma unroll
-    for (int e = 0; e < VE; ++e) {
-        dhe[e] = ca.gk + e < kend ? kh * p.cdh : -(1 << 30);   // k past kend: an out-of-range row
-        dwe[e] = kw * p.cdw;
-        koff[e] = ((int64_t)(kh * p.cdh) * p.cW + dwe[e]) * p.cC + ci;
-        if (++ci == p.cC) {
-            ci = 0;
-            if (++kw == p.cKW) {
-                kw = 0;
-                ++kh;
-            }
-        }
-    }
-    // With unit dilation along the width, the KW x Cin elements of one filter
-    // row are contiguous in the NHWC image (k = kw Cin + ci maps to kw Cin + ci
-    // elements past the row's first tap): a chunk that stays within one filter
-    // row, below kend, whose first and last taps fall inside the image, is one
-    // 16-byte (unaligned) load.  The chunk's first tap is at column ca.kw, its
-    // last at kw_last (same row ca.kh).
-    const int run = p.cKW * p.cC;                  // elements of one filter row
-    const int j0 = ca.kw * p.cC + ca.ci;           // the chunk's first element within its row
-    const bool one_row = p.cdw == 1 && j0 + VE <= run && ca.gk + VE <= kend;
-    const int kw_last = (j0 + VE - 1) / p.cC;
-#pragma unroll
-    for (int v = 0; v < AV; ++v) {
-        unsigned e16[VE];
-        if (one_row && (unsigned)(ca.ih0[v] + dhe[0]) < (unsigned)p.cH && ca.iw0[v] + dwe[0] >= 0 &&
-            ca.iw0[v] + kw_last < p.cW) {
-            ra[v] = ld_g<u32x4_u>(X + (ca.pix[v] + koff[0]) * EB);
-            continue;
-        }
-#pragma unroll
-        for (int e = 0; e < VE; ++e) {
-            unsigned val = 0u;
-            if ((unsigned)(ca.ih0[v] + dhe[e]) < (unsigned)p.cH && (unsigned)(ca.iw0[v] + dwe[e]) < (unsigned)p.cW) {
-                const char* src = X + (ca.pix[v] + koff[e]) * EB;
-                val = H ? (unsigned)ld_g<uint16_t>(src) : ld_g<unsigned>(src);
-            }
-            e16[e] = val;
-        }
-        u32x4 x;
-        if (H) {
-#pragma unroll
-            for (int e = 0; e < 8; e += 2)
-                x[e >> 1] = pack2(e16[e], e16[e + 1]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                x[e] = e16[e];
-        }
-        ra[v] = x;
-    }
-}
-
 // x shifted down by s bytes (zeros from above), s >= 0.
 __device__ __forceinline__ u32x4 shr_bytes(const u32x4& x, int s)
 {
@@ -229,6 +145,176 @@ __device__ __forceinline__ u32x4 keep_elems(const u32x4& x, int valid)
             y[d] = 2 * d + 1 < valid ? x[d] : 2 * d < valid ? x[d] & 0xffffu : 0u;
     }
     return y;
+}
+// x shifted by s bytes: down for s >= 0, up (zeros from below) for s < 0.
+__device__ __forceinline__ u32x4 shift_bytes(const u32x4& x, int s)
+{
+    const uint64_t lo = (uint64_t)x[0] | (uint64_t)x[1] << 32, hi = (uint64_t)x[2] | (uint64_t)x[3] << 32;
+    const int t = -s * 8;
+    const uint64_t l = t < 64 ? lo << (t & 63) : 0;
+    const uint64_t h = t < 64 ? hi << (t & 63) | (lo >> 1) >> (63 - (t & 63)) : t < 128 ? lo << (t & 63) : 0;
+    const u32x4 d = shr_bytes(x, max(s, 0)), u = {(unsigned)l, (unsigned)(l >> 32), (unsigned)h, (unsigned)(h >> 32)};
+    return s >= 0 ? d : u;
+}
+
+// A of a convolution for one K step, in registers on its way into LDS.  The
+// chunks are loaded without a branch, each from addresses that lie inside the
+// image, and put right when the step goes to LDS (conv_finish): a predicated
+// load into zeroed registers makes the compiler wait for every load in flight
+// before it issues the next, and the gather is bound by the latency of those
+// round trips.  fp16, 16 x 224 x 224 x 3 into 64, 7 x 7, stride 2 (a third of
+// the chunks cross filter rows): 62.3 -> 43.7 us; a calibrated K step of
+// whole chunks on the mixed 128 x 64 tile 2.04 -> 1.55 us.
+template <int AV>
+struct ConvRegs {
+    u32x4 x[AV];    // the chunk; where it crosses into the next filter row, its part in the first one
+    u32x4 y[AV];    // ... and its part in the next
+    int fix[AV];    // 0: x as loaded; else conv_fix's fields
+};
+// What a loaded chunk needs: shifts of x and y by elements (negative: up), the
+// elements of x that count (the rest come from y), and the elements that count at all.
+template <int VE>
+__device__ __forceinline__ int conv_fix(int dx, int dy, int nx, int keep)
+{
+    return (dx & 31) | (dy & 31) << 5 | (VE - nx) << 10 | (VE - keep) << 14;
+}
+template <int AV, int VE, int EB>
+__device__ __forceinline__ void conv_finish(ConvRegs<AV>& c)
+{
+#pragma unroll
+    for (int v = 0; v < AV; ++v) {
+        const int f = c.fix[v];
+        if (__builtin_amdgcn_ballot_w64(f != 0) == 0)    // wave-uniform
+            continue;
+        u32x4 x = c.x[v];
+        if (__builtin_amdgcn_ballot_w64((f & 0x3fff) != 0) != 0) {
+            const int nx = VE - ((f >> 10) & 15);
+            x = keep_elems<EB>(shift_bytes(x, (f << 27 >> 27) * EB), nx);
+            const u32x4 y = shift_bytes(c.y[v], (f << 22 >> 27) * EB);
+            x |= y ^ keep_elems<EB>(y, nx);
+        }
+        c.x[v] = keep_elems<EB>(x, VE - ((f >> 14) & 15));
+    }
+}
+
+// A of a convolution for one K step: the chunk column held in `ca` (see
+// ConvA) of AV rows, gathered from the image X through the im2col map.  Row gm
+// of the implicit A is output pixel (n, oh, ow); column gk is filter tap
+// (kh, kw) and input channel ci, with gk = (kh * KW + kw) * Cin + ci.  When
+// Cin is a multiple of the chunk, a chunk never straddles two taps and is one
+// 16-byte load (or zeros in the padding).  Otherwise it is one or two loads
+// where the filter row is contiguous in the image (see below), else gathered
+// element by element.  Taps in the padding and k at or past kend read as zeros.
+template <class CA, int AV, int VE, bool H, int EB>
+__device__ __forceinline__ void conv_gather(const VxGemmArgs& p, const char* __restrict__ X, const CA& ca, int kend,
+                                            ConvRegs<AV>& out)
+{
+    u32x4 (&ra)[AV] = out.x;
+#pragma unroll
+    for (int v = 0; v < AV; ++v) {
+        out.y[v] = u32x4{0, 0, 0, 0};
+        out.fix[v] = 0;
+    }
+    if (p.cH <= 0 || p.cW <= 0) {   // an image without a pixel: every tap is padding
+#pragma unroll
+        for (int v = 0; v < AV; ++v)
+            ra[v] = u32x4{0, 0, 0, 0};
+        return;
+    }
+    if (p.cC % VE == 0) {   // wave-uniform: a chunk is VE channels of one tap
+        const int dh = ca.kh * p.cdh, dw = ca.kw * p.cdw;
+        const int64_t koff = ((int64_t)dh * p.cW + dw) * p.cC + ca.ci;
+        const bool kin = ca.gk < kend;
+#pragma unroll
+        for (int v = 0; v < AV; ++v) {
+            const bool in =
+                kin && (unsigned)(ca.ih0[v] + dh) < (unsigned)p.cH && (unsigned)(ca.iw0[v] + dw) < (unsigned)p.cW;
+            ra[v] = ld_g<u32x4_u>(X + (in ? ca.pix[v] + koff : 0) * EB);
+            out.fix[v] = in ? 0 : conv_fix<VE>(0, 0, VE, 0);
+        }
+        return;
+    }
+    // With unit dilation along the width, the KW x Cin elements of one filter
+    // row are contiguous in the NHWC image (k = kw Cin + ci maps to kw Cin + ci
+    // elements past the row's first tap).  A chunk no longer than a filter row
+    // lies in one or two of them: each part is one (unaligned) load at the
+    // place in its image row where the chunk's first element would be, kept
+    // inside the row and shifted by what that moved it, which also brings the
+    // zeros of the padding left and right of the image.  The second load only
+    // goes out where a lane of the wave crosses filter rows.
+    const int run = p.cKW * p.cC;                  // elements of one filter row
+    const int j0 = ca.kw * p.cC + ca.ci;           // the chunk's first element within its row
+    const int64_t row_elems = (int64_t)p.cW * p.cC;
+    if (p.cdw == 1 && run >= VE && row_elems >= VE && ((int64_t)p.cW + 2 * (int64_t)p.cpw) * p.cC < (1 << 30)) {
+        const int end = (int)row_elems - VE;       // the last chunk of an image row
+        const int nx = min(VE, run - j0);
+        const int keep = max(0, min(VE, kend - ca.gk));
+        const bool cross = keep > nx;
+        const int64_t koff = (int64_t)(ca.kh * p.cdh) * row_elems, knext = (int64_t)p.cdh * row_elems;
+#pragma unroll
+        for (int v = 0; v < AV; ++v) {
+            const int ih = ca.ih0[v] + ca.kh * p.cdh, iw = ca.iw0[v] * p.cC;
+            const bool in = keep > 0 && (unsigned)ih < (unsigned)p.cH;
+            const int at = iw + j0, from = max(0, min(at, end));
+            ra[v] = ld_g<u32x4_u>(X + (in ? ca.pix[v] + koff + (from - iw) : 0) * EB);
+            // (no element of x counts: shifted out whole)
+            out.fix[v] = in ? conv_fix<VE>(max(-VE, min(at - from, VE)), 0, cross ? nx : VE, keep)
+                            : conv_fix<VE>(cross ? VE : 0, 0, cross ? nx : VE, cross ? keep : 0);
+        }
+        if (__builtin_amdgcn_ballot_w64(cross) != 0) {
+#pragma unroll
+            for (int v = 0; v < AV; ++v) {
+                const int ih = ca.ih0[v] + (ca.kh + 1) * p.cdh, iw = ca.iw0[v] * p.cC;
+                const bool in = cross && (unsigned)ih < (unsigned)p.cH;
+                const int at = iw + j0 - run, from = max(0, min(at, end));
+                out.y[v] = ld_g<u32x4_u>(X + (in ? ca.pix[v] + koff + knext + (from - iw) : 0) * EB);
+                out.fix[v] |= (in ? max(-VE, min(at - from, VE)) & 31 : cross ? VE : 0) << 5;
+            }
+        }
+        return;
+    }
+    // a filter dilated along the width, or shorter than a chunk: the VE elements
+    // of a chunk walk over channels, then filter columns, then filter rows
+    int ci = ca.ci, kw = ca.kw, kh = ca.kh;
+    int dhe[VE], dwe[VE];
+    int64_t koff[VE];
+#pragma unroll
+    for (int e = 0; e < VE; ++e) {
+        dhe[e] = ca.gk + e < kend ? kh * p.cdh : -(1 << 30);   // k past kend: an out-of-range row
+        dwe[e] = kw * p.cdw;
+        koff[e] = ((int64_t)(kh * p.cdh) * p.cW + dwe[e]) * p.cC + ci;
+        if (++ci == p.cC) {
+            ci = 0;
+            if (++kw == p.cKW) {
+                kw = 0;
+                ++kh;
+            }
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < AV; ++v) {
+        unsigned e16[VE];
+#pragma unroll
+        for (int e = 0; e < VE; ++e) {
+            unsigned val = 0u;
+            if ((unsigned)(ca.ih0[v] + dhe[e]) < (unsigned)p.cH && (unsigned)(ca.iw0[v] + dwe[e]) < (unsigned)p.cW) {
+                const char* src = X + (ca.pix[v] + koff[e]) * EB;
+                val = H ? (unsigned)ld_g<uint16_t>(src) : ld_g<unsigned>(src);
+            }
+            e16[e] = val;
+        }
+        u32x4 x;
+        if (H) {
+#pragma unroll
+            for (int e = 0; e < 8; e += 2)
+                x[e >> 1] = pack2(e16[e], e16[e + 1]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                x[e] = e16[e];
+        }
+        ra[v] = x;
+    }
 }
 
 // One K step of one operand for the branch-free loads: the scalar base, and
@@ -299,6 +385,7 @@ struct Tile {
     // LDS store.
     u32x4 ra[C::AV];
     u32x4 rb[C::H ? C::BBLK * C::BK : C::BV];
+    ConvRegs<C::CONV ? C::AV : 1> rc;   // a convolution's A
 
     // Global -> registers for the K step starting at k0 (< kend).  Every
     // thread moves 16-byte chunks of a row (8 elements of 16-bit data, 4 of
@@ -442,7 +529,7 @@ struct Tile {
     __device__ __forceinline__ void load_a_conv(const VxGemmArgs& p, const char* __restrict__ X, const CA& ca,
                                                 int kend)
     {
-        conv_gather<CA, C::AV, C::VE, C::H, C::EB>(p, X, ca, kend, ra);
+        conv_gather<CA, C::AV, C::VE, C::H, C::EB>(p, X, ca, kend, rc);
     }
 
     // The first `valid` (< one chunk) elements of a row chunk, zeros after.
@@ -469,11 +556,18 @@ struct Tile {
     {
         char* As = stage;
         char* Bs = stage + C::A_ELEMS * C::EB;
+        if constexpr (C::CONV)
+            conv_finish<C::AV, C::VE, C::EB>(rc);
 #pragma unroll
         for (int v = 0; v < C::AV; ++v) {
             const int idx = t + v * C::NT;
             const int r = idx / (C::KB / C::VE), c = idx % (C::KB / C::VE);
-            *(u32x4*)(As + (r * C::LDA + c * C::VE) * C::EB) = ra[v];
+            u32x4 x;
+            if constexpr (C::CONV)
+                x = rc.x[v];
+            else
+                x = ra[v];
+            *(u32x4*)(As + (r * C::LDA + c * C::VE) * C::EB) = x;
         }
         if (C::H) {
             // transpose each BK x 8 block into 8 k-vectors (one per column)

@@ -52,8 +52,8 @@ struct VxShape {
     int op = 0;    // 0: GEMM; 1: 2-D convolution as an implicit GEMM (conv kernels only)
     int64_t a_bytes = 0;   // convolution: bytes of the image (the direct-to-LDS kernels need < 2^31)
     // convolution: the share of the image's 16-byte chunks that the kernels
-    // gathering the image through VGPRs load element by element (0 when the
-    // channels come in whole chunks)
+    // gathering the image through VGPRs load element by element or in two parts
+    // (0 when the channels come in whole chunks)
     double gather_frac = 0.0;
 };
 
